@@ -38,3 +38,32 @@ def test_passes_share_their_logits(D, G, N):
     torch.cuda.synchronize()
     s, d = pb.lse.cpu().numpy()[clear], lse.cpu().numpy()[clear]
     assert np.array_equal(s, d), f"{(s != d).sum()} of {s.size} normalisers differ"
+
+
+@pytest.mark.parametrize("D,G", [(32, 64), (64, 32)])
+def test_linearno_backward_keeps_the_column_normaliser_apart(D, G):
+    """LinearNO's weights are 2^(t - clse) with clse near 13 at 2^13 points. Subtracted from the
+    finished logit it costs one rounding: uniform within 2^-21 for differences up to 16, so a weight
+    is off by ln 2 * 2^-21 / sqrt(3) = 1.9e-7 in the mean square, the logit and clse add as much
+    each, dz and z a few units of fp32 (4e-7): 6e-7 in all, 8e-7 allowed. As the start value of the
+    products it cut every part product at 2^-20 and came to 1.1e-6 and more."""
+    from paper_2609_32525_amd.runner import PathBuffers
+    from paritycheck import measures
+    w = small(f"lno_D{D}_G{G}", "f32", D, G, O.MIX_LINEAR_C, N=1 << 13, B=1, H=2,
+              tau_mode="uniform")
+    announce(f"linearno normaliser {w}")
+    inp, ut = W.make_inputs(w), W.untied_params(w)
+    pb = PathBuffers(inp, w.mix, w.dtype, w.eps, untied=ut, linearno=True)
+    pb.step()
+    got = pb.results()
+    prm = {k: inp.get(k) for k in ("A", "Wc", "Wq", "Wk", "Wv", "scale")}
+    args = (inp["x"], inp["fx"], inp["Ws"], inp["b"], inp["tau"], ut["Wd"], ut["bd"], ut["taud"],
+            w.mix, prm)
+    bwd = O.linearno_backward(*args, inp["dout"], fwd=O.linearno_forward(*args))
+    bad = {}
+    for k in ("dfx", "dWs"):
+        n, _ = measures(got[k], bwd[k], 4.0)
+        print(f"  {k}: {n:.2e}", flush=True)
+        if not n <= 8e-7:
+            bad[k] = n
+    assert not bad, bad
