@@ -234,6 +234,18 @@ __device__ __forceinline__ f4 mfma4(float a, float b, f4 c) {
 }
 __device__ __forceinline__ f4 zero4() { return f4{0.f, 0.f, 0.f, 0.f}; }
 
+// A product's sum over k in four chains, MFMA k index r on chain r: an MFMA rounds its running
+// sum, and one chain of 16 for 64 columns left the attention's zmix 1.1 to 1.4 times as far from
+// 64 bits (G = 32 to 64, V = 64).
+struct Chains {
+  f4 c[4];
+  __device__ __forceinline__ Chains() {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) c[r] = zero4();
+  }
+  __device__ __forceinline__ f4 sum() const { return (c[0] + c[1]) + (c[2] + c[3]); }
+};
+
 struct GemmDesc {
   // element (m, k) of A for output o and summand s: A[(o % a_mod) * a_o + s * a_s + m * a_rs + k * a_cs]
   const float* A;
@@ -276,7 +288,7 @@ __global__ __launch_bounds__(64 * kGemmWaves) void k_tile_gemm(GemmDesc d) {
   };
   // blocks wave, wave + 4, ...; four at a time, their loads issued together (blocks past the
   // end reload the last one and are not multiplied)
-  f4 acc0 = zero4(), acc1 = zero4();
+  Chains c;
   for (int q = wave; q < nb; q += 4 * kGemmWaves) {
     f4 av[4], bv[4];
 #pragma unroll
@@ -284,12 +296,11 @@ __global__ __launch_bounds__(64 * kGemmWaves) void k_tile_gemm(GemmDesc d) {
 #pragma unroll
     for (int u = 0; u < 4; ++u)
       if (q + u * kGemmWaves < nb) {
-        f4& acc = (u & 1) ? acc1 : acc0;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc = mfma4(av[u][r], bv[u][r], acc);
+        for (int r = 0; r < 4; ++r) c.c[r] = mfma4(av[u][r], bv[u][r], c.c[r]);
       }
   }
-  red[wave][lane] = acc0 + acc1;
+  red[wave][lane] = c.sum();
   __syncthreads();
   if (wave != 0) return;
   f4 sum = red[0][lane];
@@ -444,12 +455,27 @@ __device__ __forceinline__ Row<V> ld_row(const float* p, int j) {
 // C[m][n] = a_m . b_n over V columns.
 template <int V>
 __device__ __forceinline__ f4 row_dot(const Row<V>& a, const Row<V>& b) {
-  f4 c0 = zero4(), c1 = zero4();
+  Chains c;
 #pragma unroll
   for (int mt = 0; mt < V / 16; ++mt)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) (r & 1 ? c1 : c0) = mfma4(a.v[mt][r], b.v[mt][r], r & 1 ? c1 : c0);
-  return c0 + c1;
+    for (int r = 0; r < 4; ++r) c.c[r] = mfma4(a.v[mt][r], b.v[mt][r], c.c[r]);
+  return c.sum();
+}
+// C[m][n] = sum over e of W[e][16 nt + m] b_n[e].
+template <int V>
+__device__ __forceinline__ f4 col_dot(const float* W, int nt, const Row<V>& b, int i, int j) {
+  float w[V / 16][4];
+#pragma unroll
+  for (int mt = 0; mt < V / 16; ++mt)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) w[mt][r] = W[(16 * mt + 4 * j + r) * V + 16 * nt + i];
+  Chains c;
+#pragma unroll
+  for (int mt = 0; mt < V / 16; ++mt)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) c.c[r] = mfma4(w[mt][r], b.v[mt][r], c.c[r]);
+  return c.sum();
 }
 // acc[ct] += (tile)^T M: the tile's rows are tokens t0 + 4 j + r, M their V-wide rows.
 template <int V>
@@ -464,14 +490,7 @@ template <int V>
 __device__ __forceinline__ Row<V> project(const Row<V>& z, const float* W, int i, int j) {
   Row<V> o;
 #pragma unroll
-  for (int nt = 0; nt < V / 16; ++nt) {
-    f4 acc = zero4();
-#pragma unroll
-    for (int mt = 0; mt < V / 16; ++mt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc = mfma4(W[(16 * mt + 4 * j + r) * V + 16 * nt + i], z.v[mt][r], acc);
-    o.v[nt] = acc;
-  }
+  for (int nt = 0; nt < V / 16; ++nt) o.v[nt] = col_dot<V>(W, nt, z, i, j);
   return o;
 }
 // (rows W^T)^T as a Row.
@@ -495,8 +514,9 @@ __device__ __forceinline__ float rows_max(float v) {
 // Forward. Scores come from r = (z Wq) Wk^T (S[g][u] = scale r_g . z_u, so k is never formed),
 // each wavefront keeping its TPW score tiles in registers between the softmax statistics and
 // the weights; T = P z and zmix = T Wv (= P v by associativity).
+// (Few workgroups per compute unit: registers for loads in flight count, not occupancy.)
 template <int V, int NW, int TPW>
-__global__ __launch_bounds__(64 * NW) void k_attn_rows(const float* z, float* zmix, float* P,
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 4))) void k_attn_rows(const float* z, float* zmix, float* P,
                                                        const float* Wq, const float* Wk,
                                                        const float* Wv, float scale, int G) {
   constexpr int VT = V / 16;
@@ -573,12 +593,7 @@ __global__ __launch_bounds__(64 * NW) void k_attn_rows(const float* z, float* zm
       for (int q = 0; q < NW; ++q)
         t.v[mt] += *reinterpret_cast<const f4*>(&red[q][i * kRowPad<V> + 16 * mt + 4 * j]);
     }
-    f4 acc = zero4();
-#pragma unroll
-    for (int mt = 0; mt < VT; ++mt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc = mfma4(Wv[(16 * mt + 4 * j + r) * V + 16 * n + i], t.v[mt][r], acc);
-    *reinterpret_cast<f4*>(zmix + ((int64_t)bh * G + g0 + i) * V + 16 * n + 4 * j) = acc;
+    *reinterpret_cast<f4*>(zmix + ((int64_t)bh * G + g0 + i) * V + 16 * n + 4 * j) = col_dot<V>(Wv, n, t, i, j);
   }
 }
 
@@ -648,9 +663,10 @@ __global__ __launch_bounds__(512) void k_attn_bwd_rows(
   const float* Pb = P + tb * G;
   const float* Db = D + tb;
   const float* gz = dzm + tb * V;
-  f4 a0[VT], a1[VT];
+  // (two chains each: at G = 1024 one takes 64 MFMAs)
+  f4 a0[2][VT], a1[2][VT];
 #pragma unroll
-  for (int ct = 0; ct < VT; ++ct) a0[ct] = a1[ct] = zero4();
+  for (int ct = 0; ct < VT; ++ct) a0[0][ct] = a0[1][ct] = a1[0][ct] = a1[1][ct] = zero4();
   // the next tile's operands are loaded before a tile is multiplied (tiles past the end reload
   // the last one)
   if (w < 4) {
@@ -684,7 +700,7 @@ __global__ __launch_bounds__(512) void k_attn_bwd_rows(
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int ct = 0; ct < VT; ++ct) a0[ct] = mfma4(dS[r], kc[r][ct], a0[ct]);
+        for (int ct = 0; ct < VT; ++ct) a0[r & 1][ct] = mfma4(dS[r], kc[r][ct], a0[r & 1][ct]);
     }
   } else {
     const Row<V> vr = ld_row<V>(v + (tb + g0 + i) * V, j);
@@ -725,8 +741,8 @@ __global__ __launch_bounds__(512) void k_attn_bwd_rows(
       for (int r = 0; r < 4; ++r)
 #pragma unroll
         for (int ct = 0; ct < VT; ++ct) {
-          a0[ct] = mfma4(dS[r], qc[r][ct], a0[ct]);
-          a1[ct] = mfma4(p[r], zc[r][ct], a1[ct]);
+          a0[r & 1][ct] = mfma4(dS[r], qc[r][ct], a0[r & 1][ct]);
+          a1[r & 1][ct] = mfma4(p[r], zc[r][ct], a1[r & 1][ct]);
         }
     }
   }
@@ -735,8 +751,8 @@ __global__ __launch_bounds__(512) void k_attn_bwd_rows(
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int at = (4 * j + r) * VP + 16 * ct + i;
-      red[sub][w < 4 ? 0 : 1][at] = a0[ct][r];
-      if (w >= 4) red[sub][2][at] = a1[ct][r];
+      red[sub][w < 4 ? 0 : 1][at] = a0[0][ct][r] + a0[1][ct][r];
+      if (w >= 4) red[sub][2][at] = a1[0][ct][r] + a1[1][ct][r];
     }
   __syncthreads();
   for (int idx = threadIdx.x; idx < 3 * 16 * V; idx += 512) {

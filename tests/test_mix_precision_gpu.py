@@ -1,0 +1,49 @@
+"""Rounding of the token mixes beyond one workgroup, on their own (needs an MI355X): their sums
+run in several short chains, since a matrix instruction rounds its running sum."""
+import math
+
+import pytest
+
+from paritycheck import announce
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kind,G,V,bound", [("attn", 64, 64, 1.3e-7), ("linear_c", 512, 16, 6.5e-8)])
+def test_mix_sums_in_short_chains(kind, G, V, bound):
+    """zmix against 64 bits, normwise over 6 samples (the spread between samples is 1%). u = 6e-8
+    is the fp32 unit. linear_c: sums of 16 in four chains of one instruction, joined in two steps,
+    and the store: three roundings, u / sqrt(3) each at most, 6.0e-8; one chain of four
+    instructions rounds once more on the whole sum (7.3e-8). Attention over nearly equal tokens: the
+    product with W_v over 64 columns sets the error, four chains of four instructions
+    (1.1e-7) against one of sixteen (1.6e-7)."""
+    import torch
+    import paper_2609_32525_amd as fs
+    announce(f"mix precision {kind} G={G} V={V}")
+    B, H = 1, 4
+    err = []
+    for seed in range(6):
+        g = torch.Generator(device="cuda")
+        g.manual_seed(seed)
+        lim = math.sqrt(6.0 / (2 * V))
+        W = [(torch.rand(V, V, device="cuda", generator=g) * 2 - 1) * lim for _ in range(3)]
+        z = torch.randn(B, H, G, V, device="cuda", generator=g)
+        if kind == "attn":
+            z = z * 0.03 + torch.randn(B, H, 1, V, device="cuda", generator=g)
+        z = z.contiguous()
+        prob = fs.Problem.make(B, 64, H, V, V, G, fs.F32, 1e-5, 0)
+        md = fs.MixDesc.make(fs.MIX_ATTN if kind == "attn" else fs.MIX_LINEAR_C, Wc=W[0], Wq=W[0],
+                             Wk=W[1], Wv=W[2], scale=1.0 / math.sqrt(V))
+        zmix = torch.empty_like(z)
+        fs.mix(prob, md, z, zmix, torch.empty(B, H, G, G, device="cuda") if kind == "attn" else None)
+        torch.cuda.synchronize()
+        zd, Wd = z.double().cpu(), [w.double().cpu() for w in W]
+        if kind == "attn":
+            P = torch.softmax((zd @ Wd[0]) @ (zd @ Wd[1]).transpose(2, 3) / math.sqrt(V), -1)
+            ref = P @ (zd @ Wd[2])
+        else:
+            ref = zd @ Wd[0]
+        err.append(float((zmix.double().cpu() - ref).norm() / ref.norm()))
+    mean = sum(err) / len(err)
+    print(f"  zmix {mean:.2e}", flush=True)
+    assert mean <= bound, err
