@@ -467,9 +467,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
         for (int pb = 0; pb < 2; ++pb) t[gb][pb] = mm_slot_row<BF, D, 4, BF>(wop, gb, xo[pb], bT);
       }
     };
-    // bf16: sums against the first slot's logit (as in k_slice: at least 1, and exact until far
-    // beyond 2^100), with no maxima; G = 1024:
-    // 468 -> 398 us, G = 256: 141 -> 127 us
+    // bf16: sums against sum_ref of the first slot's logit (as in k_slice), with no maxima;
+    // G = 1024: 468 -> 398 us, G = 256: 141 -> 127 us
     bool ok = BF;
     if constexpr (BF) {
       for (int blk = 0; blk < NB; ++blk) {
@@ -477,7 +476,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
         logits(blk, t);
 #pragma unroll
         for (int pb = 0; pb < 2; ++pb) {
-          if (blk == 0) m[pb] = __shfl(t[0][pb][0], i);  // slot 0 lies in lane row 0
+          if (blk == 0) m[pb] = sum_ref(__shfl(t[0][pb][0], i));  // slot 0 lies in lane row 0
           float sum = 0.f;
 #pragma unroll
           for (int gb = 0; gb < 4; ++gb)
@@ -515,7 +514,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
 #pragma unroll
     for (int pb = 0; pb < 2; ++pb) {
       const float L = col4_sum(l[pb]);
-      if (j == 0) bst32(rl, m[pb] + __log2f(L), 4 * i, 4 * (tp0 + 16 * pb));
+      if (j == 0) bst32(rl, BF ? ref_lse(m[pb], L) : m[pb] + __log2f(L), 4 * i, 4 * (tp0 + 16 * pb));
     }
   }
 }

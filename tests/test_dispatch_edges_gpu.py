@@ -37,6 +37,36 @@ def test_first_slot_far_below(D, G, b0):
     c.finish()
 
 
+@pytest.mark.parametrize("D,G", [(32, 64), (16, 32), (32, 256), (16, 1024)])
+def test_reference_costs_no_bits(D, G):
+    """The reference must not cost the normaliser its last bits: with the first slot 60 below the
+    others (base 2) and logits that bf16 operands hold exactly (projections of 8 significant bits,
+    tau = log2 e), lse of order 6 to 11 is off by half an ulp (2^-21 = 4.8e-7 at most), by the rounding
+    of the running logits and of the projections' two bf16 parts (2^-17 of a part below 2^-8 of the
+    logit), of the same size, and by the exponentials', which average out: 7e-7 allowed in the root mean
+    square. Differences from the first logit itself are of order 64 to 70 and their sum's logarithm
+    rounds at 2^-17: 4e-6."""
+    import torch
+    import paper_2609_32525_amd as fs
+    w = small(f"ref_bits_D{D}_G{G}", "bf16", D, G, O.MIX_IDENTITY, N=2000, H=2, B=1)
+    announce(f"reference {w}")
+    inp = W.make_inputs(w)
+    inp["Ws"] = W.round_to_bf16(inp["Ws"])
+    inp["tau"] = np.full(2, 1.0 / LN2, np.float32)
+    inp["b"] = np.zeros(G, np.float32)
+    inp["b"][0] = -60.0
+    pb, got = run_gpu(w, inp, backward=False)
+    a = (inp["x"].astype(np.float64).transpose(0, 2, 1, 3) @ inp["Ws"].astype(np.float64) +
+         inp["b"]) / (inp["tau"].astype(np.float64)[:, None, None] * LN2)
+    ref = a.max(-1) + np.log2(np.exp2(a - a.max(-1)[..., None]).sum(-1))
+    lse, out = torch.empty_like(pb.lse), torch.empty_like(pb.out)
+    fs.deslice_stats_fwd(pb.prob, pb.x, pb.Ws, pb.b, pb.tau, pb.zmix, lse, out)
+    torch.cuda.synchronize()
+    e = [float(np.sqrt(np.mean((l.double().cpu().numpy() - ref) ** 2))) for l in (pb.lse, lse)]
+    print(f"  lse off by {e[0]:.2e} (slice) {e[1]:.2e} (stats)", flush=True)
+    assert max(e) <= 7e-7, e
+
+
 @pytest.mark.parametrize("D,G", [(32, 64), (32, 48), (64, 32)])
 @pytest.mark.parametrize("N", [1, 17, 129, 641])
 def test_fp32_parts_ragged(D, G, N):
