@@ -1,5 +1,5 @@
 """GPU parity where a kernel's choice of path can go wrong (needs an MI355X): the softmax sums
-taken against the first slot's logit, fp32 products from bf16 parts, attention among token sets
+taken against a reference other than the maximum, fp32 products from bf16 parts, attention among token sets
 beyond one workgroup. Same oracle and bar as the parity tests."""
 import numpy as np
 import pytest
@@ -12,18 +12,37 @@ from test_parity_gpu import LN2, compare, run_gpu, small
 pytestmark = pytest.mark.gpu
 
 
+def log2_sums(w, inp, h):
+    """log2 of the sums the bf16 passes accept or refuse in head h: against the first slot's
+    logit (base 2) brought to within 64 of it."""
+    x, Ws = inp["x"][:, :, h].astype(np.float64), inp["Ws"][h].astype(np.float64)
+    a = (x @ Ws + inp["b"][h]) / (inp["tau"][h] * LN2)
+    top = a.max(-1)
+    lse = top + np.log2(np.exp2(a - top[..., None]).sum(-1))
+    return lse - (a[..., 0] - np.clip(a[..., 0], -64.0, 64.0))
+
+
 @pytest.mark.parametrize("D,G", [(16, 32), (32, 64), (64, 64), (32, 256), (16, 1024)])
-@pytest.mark.parametrize("b0", [-40.0, -600.0])
-def test_first_slot_far_below(D, G, b0):
-    """bf16 sums the weights against the first slot's logit while the sum stays below 2^100, and
-    with the maxima where it does not: the other slots lie 40 / tau (inside) or 600 / tau
-    (beyond) above it, for one head only, so both kinds of tiles meet in one launch."""
+@pytest.mark.parametrize("b0,side", [(-20.0, "inside"), (-40.0, "inside"), (600.0, "inside"),
+                                     (-53.5, "both"), (-600.0, "beyond")])
+def test_first_slot_far_off(D, G, b0, side):
+    """bf16 sums a point's weights against a reference from its first slot's logit while the sum
+    stays below 2^100, and against the maximum where it does not. One head's first slot is set
+    b0 / tau off the others: near enough for reference 0 (-20), sums of 2^50 and more that are
+    accepted (-40), the first slot far above (600), accepted and refused points in one tile
+    (-53.5), every point refused (-600). The other heads are ordinary, so accepted and redone
+    tiles meet in one launch."""
     import torch
     import paper_2609_32525_amd as fs
     w = small(f"first_slot_D{D}_G{G}", "bf16", D, G, O.MIX_LINEAR_G, N=333, ws_per_head=True)
-    announce(f"first slot {b0} below: {w}")
+    announce(f"first slot {b0} off: {w}")
     inp = W.make_inputs(w)
     inp["b"][1, 0] = b0
+    l = log2_sums(w, inp, 1)
+    # (1 away from the limit on the sides that must be clear)
+    assert {"inside": l.max() < 99.0, "beyond": l.min() > 101.0,
+            "both": l.min() < 99.0 and l.max() > 101.0}[side], (l.min(), l.max())
+    assert b0 != -40.0 or l.min() > 49.0
     pb, got = run_gpu(w, inp, backward=False)
     ref, _ = O.run_inputs(inp, w.mix, w.eps, backward_too=False)
     c = Checker(f"first_slot/{w.name}/{b0}", "bf16")
