@@ -20,11 +20,6 @@ constexpr int kRowGroups = kRedThreads / kCols;
 constexpr int kColsWide = 16;      // long reductions (over samples, heads and chunks)
 constexpr int kRowGroupsWide = kRedThreads / kColsWide;
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) v += __shfl_xor(v, off);
-  return v;
-}
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) v = fmaxf(v, __shfl_xor(v, off));
@@ -622,22 +617,45 @@ __global__ __launch_bounds__(192) void k_attn_qkv(const float* z, const float* z
   }
 }
 
-// D_g = sum_u P[g][u] (dzmix_g . v_u) where no zmix is at hand; one wavefront per token.
-__global__ __launch_bounds__(256) void k_attn_rowdot(const float* P, const float* dzm,
-                                                     const float* v, float* D, int64_t tokens,
-                                                     int G, int V) {
-  const int lane = threadIdx.x & 63;
-  const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (t >= tokens) return;
-  const float* vb = v + (t / G) * G * V;
-  float acc = 0.f;
-  for (int u = lane; u < G; u += 64) {
-    float d = 0.f;
-    for (int c = 0; c < V; ++c) d += dzm[t * V + c] * vb[(int64_t)u * V + c];
-    acc += P[t * G + u] * d;
+// D_g = sum_u P[g][u] (dzmix_g . v_u) where no zmix is at hand (fs_mix_bwd): a workgroup per 16
+// tokens, its wavefronts over every eighth tile of u, dP a tile product as in k_attn_bwd_rows. (One
+// wavefront per token with a dot product per lane loaded v uncoalesced, V loads a lane and
+// token: fs_mix_bwd at G = 1024, V = 32, 8 heads 538 -> 65 us.) D is subtracted from dP values of its own
+// size, so its sum goes up a tree.
+constexpr int kDotWaves = 8;
+
+template <int V>
+__global__ __launch_bounds__(64 * kDotWaves) void k_attn_rowdot(const float* P, const float* dzm,
+                                                                const float* v, float* D, int G) {
+  __shared__ float red[kDotWaves][16];
+  const int lane = threadIdx.x & 63, i = lane & 15, j = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nt = G >> 4;
+  const int bh = blockIdx.x / nt, g0 = (blockIdx.x % nt) << 4;
+  const int64_t tb = (int64_t)bh * G;  // token 0 of this (b, h)
+  const Row<V> gr = ld_row<V>(dzm + (tb + g0 + i) * V, j);
+  const float* Pg = P + (tb + g0 + i) * G + 4 * j;
+  const float* vb = v + (tb + i) * V;
+  f4 part = zero4();
+#pragma unroll 2
+  for (int t = w; t < nt; t += kDotWaves) {  // rows u = 16 t + 4 j + r, columns g = g0 + i
+    const f4 p = *reinterpret_cast<const f4*>(Pg + 16 * t);
+    const f4 dP = row_dot<V>(ld_row<V>(vb + 16 * t * V, j), gr);
+    part += p * dP;
   }
-  acc = wave_sum(acc);
-  if (lane == 0) D[t] = acc;
+  const float acc = rows_sum((part[0] + part[1]) + (part[2] + part[3]));
+  if (j == 0) red[w][i] = acc;
+  __syncthreads();
+  if (threadIdx.x < 16) {
+    float t[kDotWaves];
+#pragma unroll
+    for (int q = 0; q < kDotWaves; ++q) t[q] = red[q][threadIdx.x];
+#pragma unroll
+    for (int n = kDotWaves / 2; n > 0; n /= 2)
+#pragma unroll
+      for (int q = 0; q < n; ++q) t[q] += t[q + n];
+    D[tb + g0 + threadIdx.x] = t[0];
+  }
 }
 
 // Backward for 16 tokens of one (b, h). Wavefronts 0-3 take the tokens as rows g
@@ -907,8 +925,7 @@ static hipError_t attn_rows_bwd(const Geom& g, const MixArgs& m, const float* z,
                      v, D);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && zmix == nullptr) {
-    hipLaunchKernelGGL(k_attn_rowdot, dim3(blocks(tokens, 4)), dim3(256), 0, st, P, dzm, v, D,
-                       tokens, g.G, V);
+    hipLaunchKernelGGL((k_attn_rowdot<V>), grid, dim3(64 * kDotWaves), 0, st, P, dzm, v, D, g.G);
     e = hipGetLastError();
   }
   if (e != hipSuccess) return e;

@@ -47,3 +47,38 @@ def test_mix_sums_in_short_chains(kind, G, V, bound):
     mean = sum(err) / len(err)
     print(f"  zmix {mean:.2e}", flush=True)
     assert mean <= bound, err
+
+
+def test_mix_bwd_alone_stays_a_matrix_product():
+    """fs_mix_bwd has no zmix to take the attention's row sums of dP P from; they are formed by
+    tile products like the rest: at G = 1024 the call takes 2.5 times the forward's time (21 times
+    with a dot product per lane). 8 times allowed."""
+    import torch
+    import paper_2609_32525_amd as fs
+    announce("mix_bwd alone, G=1024")
+    B, H, G, V = 1, 8, 1024, 32
+    z, dzm = (torch.randn(B, H, G, V, device="cuda") for _ in range(2))
+    W = [torch.randn(V, V, device="cuda") / math.sqrt(V) for _ in range(3)]
+    prob = fs.Problem.make(B, 64, H, V, V, G, fs.F32, 1e-5, 0)
+    md = fs.MixDesc.make(fs.MIX_ATTN, Wq=W[0], Wk=W[1], Wv=W[2], scale=1.0 / math.sqrt(V))
+    zmix, dz, P = torch.empty_like(z), torch.empty_like(z), torch.empty(B, H, G, G, device="cuda")
+    dm = torch.empty(3 * V * V, device="cuda")
+    ws = torch.empty(fs.workspace_bytes(prob, 1), device="cuda", dtype=torch.uint8)
+
+    def us(f):
+        f()
+        t = []
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(10):
+                f()
+            b.record()
+            torch.cuda.synchronize()
+            t.append(a.elapsed_time(b) * 100.0)
+        return min(t)
+
+    fwd = us(lambda: fs.mix(prob, md, z, zmix, P))
+    bwd = us(lambda: fs.mix_bwd(prob, md, z, P, dzm, dz, dm, ws))
+    print(f"  forward {fwd:.1f} us, backward {bwd:.1f} us", flush=True)
+    assert bwd < 8.0 * fwd
