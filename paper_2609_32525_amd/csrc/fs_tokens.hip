@@ -213,15 +213,17 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_params(
 
 // ---------------------------------------------------------------------------------------
 // Linear token maps for token sets too large for the single-workgroup LDS kernels: batched
-// fp32 products C_o = sum_s A_{o,s} B_{o,s} on MFMA, one workgroup per 16 x 16 output tile,
+// fp32 products C_o = sum_s A_{o,s} B_{o,s} on MFMA, a 16 x 16 output tile per workgroup or wavefront,
 // operands read straight from global memory (they are small and cache resident). A strided
 // descriptor covers the forward map, its transpose, and the parameter gradients summed over
 // samples and heads without partials.
-// These products are bound by the latency of their loads, not by bytes or flops, so the
-// workgroup's four wavefronts split the k range (their tiles are added through LDS in a fixed
-// order) and an operand whose k index is contiguous is read 16 bytes per lane: MFMA r of a
-// 16-wide k block takes k = 4 j + r from lane row j. G = 256, V = 32, 8 heads: 18.3 us per
-// product with one wavefront per tile, 4.8 us now.
+// Few such products are bound by the latency of their loads, not by bytes or flops, so four
+// wavefronts split a long k range (their tiles are added through LDS in a fixed order) and an
+// operand whose k index is contiguous is read 16 bytes per lane: MFMA r of a 16-wide k block takes
+// k = 4 j + r from lane row j. G = 256, V = 32, 8 heads: 18.3 us per product with one wavefront per
+// tile and 4-byte loads, 4.8 us now. Many are bound by how many loads are in flight: a block at a
+// time with the next one's loads ahead keeps eight wavefronts per SIMD (16384 tiles at G = 256: 44 us;
+// four blocks at a time 49 to 53).
 // ---------------------------------------------------------------------------------------
 typedef float f4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ f4 mfma4(float a, float b, f4 c) {
@@ -255,12 +257,15 @@ struct GemmDesc {
 
 constexpr int kGemmWaves = 4;
 
+// KW: wavefronts that split a tile's k range.
+template <int KW>
 __global__ __launch_bounds__(64 * kGemmWaves) void k_tile_gemm(GemmDesc d) {
-  __shared__ f4 red[kGemmWaves][64];
+  __shared__ f4 red[KW > 1 ? kGemmWaves : 1][64];
   const int lane = threadIdx.x & 63, i = lane & 15, j = lane >> 4;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wg_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wg_wave % KW;
   const int tn = d.N >> 4;
-  const int t = blockIdx.x;
+  const int t = blockIdx.x * (kGemmWaves / KW) + wg_wave / KW;
+  if (KW == 1 && t >= (d.M >> 4) * tn) return;  // whole wavefronts
   const int m0 = (t / tn) << 4, n0 = (t % tn) << 4;
   const int o = blockIdx.y;
   const float* Ao = d.A + (int64_t)(o % d.a_mod) * d.a_o + (int64_t)(m0 + i) * d.a_rs;
@@ -281,34 +286,46 @@ __global__ __launch_bounds__(64 * kGemmWaves) void k_tile_gemm(GemmDesc d) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) bv[r] = Bp[(int64_t)r * d.b_rs];
   };
-  // blocks wave, wave + 4, ...; four at a time, their loads issued together (blocks past the
-  // end reload the last one and are not multiplied)
+  // blocks wave, wave + KW, ..., each one's loads issued before the one before it is multiplied
+  // (the last reloads itself)
   Chains c;
-  for (int q = wave; q < nb; q += 4 * kGemmWaves) {
-    f4 av[4], bv[4];
+  f4 av, bv;
+  load(wave, av, bv);
+  for (int q = wave; q < nb; q += KW) {
+    f4 an, bn;
+    load(min(q + KW, nb - 1), an, bn);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) load(min(q + u * kGemmWaves, nb - 1), av[u], bv[u]);
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (q + u * kGemmWaves < nb) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) c.c[r] = mfma4(av[u][r], bv[u][r], c.c[r]);
-      }
+    for (int r = 0; r < 4; ++r) c.c[r] = mfma4(av[r], bv[r], c.c[r]);
+    av = an;
+    bv = bn;
   }
-  red[wave][lane] = c.sum();
-  __syncthreads();
-  if (wave != 0) return;
-  f4 sum = red[0][lane];
+  f4 sum = c.sum();
+  if constexpr (KW > 1) {
+    static_assert(KW == kGemmWaves, "a workgroup per tile");
+    red[wave][lane] = sum;
+    __syncthreads();
+    if (wave != 0) return;
 #pragma unroll
-  for (int w = 1; w < kGemmWaves; ++w) sum += red[w][lane];
+    for (int w = 1; w < KW; ++w) sum += red[w][lane];
+  }
   float* Co = d.C + (int64_t)o * d.c_o + n0 + i;
 #pragma unroll
   for (int r = 0; r < 4; ++r) Co[(int64_t)(m0 + 4 * j + r) * d.c_rs] = sum[r];
 }
 
+// 16-wide k blocks from which four wavefronts split a tile's k range: at 64 blocks (G = 1024,
+// V = 32) 9.2 us against 23.9 with one wavefront per tile on 512 tiles, 76.8 against 81.2 on 8192;
+// at 16 (G = 256) 44.1 against 44.7 on 16384; at 7 and 2 the split leaves wavefronts idle and costs
+// (28672 tiles of G = 112, V = 64: 44.0 against 35.7; 32768 of a channel map at V = 32: 34.5 against 17.2).
+constexpr int kSplitBlocks = 16;
+
 static hipError_t run_gemm(const GemmDesc& d, int nout, hipStream_t st) {
   const int tiles = (d.M / 16) * (d.N / 16);
-  hipLaunchKernelGGL(k_tile_gemm, dim3(tiles, nout), dim3(64 * kGemmWaves), 0, st, d);
+  if ((d.K / 16) * (int64_t)d.nsum >= kSplitBlocks)
+    hipLaunchKernelGGL(k_tile_gemm<kGemmWaves>, dim3(tiles, nout), dim3(64 * kGemmWaves), 0, st, d);
+  else
+    hipLaunchKernelGGL(k_tile_gemm<1>, dim3((tiles + kGemmWaves - 1) / kGemmWaves, nout),
+                       dim3(64 * kGemmWaves), 0, st, d);
   return hipGetLastError();
 }
 
