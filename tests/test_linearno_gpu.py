@@ -146,3 +146,30 @@ def test_linearno_full_size_volume():
         for k in ("dtau", "dtaud"):
             c.add(f"{k}[{h}]", got[k][h], bwd[k][h], keep=False)
     c.finish()
+
+
+@pytest.mark.parametrize("N", [512, 4096, 8192, 16384, 20480])
+def test_chunk_merge(N):
+    """The merge of the chunks' partials by one, four and sixteen thread groups (1, 8, 16, 32 and
+    40 chunks here), with more columns than its workgroups take in the last one (G V = 1536)."""
+    import torch
+    import paper_2609_32525_amd as fs
+    w = case(f"merge_N{N}", "f32", 32, 48, O.MIX_IDENTITY, B=1, N=N, H=2)
+    announce(f"chunk merge {w}")
+    inp = W.make_inputs(w)
+    up = lambda k: torch.from_numpy(np.ascontiguousarray(inp[k])).to("cuda:0")
+    prob = fs.Problem.make(1, N, 2, 32, 32, 48, fs.F32, w.eps, 0)
+    z, clse = torch.empty(1, 2, 48, 32, device="cuda"), torch.empty(1, 2, 48, device="cuda")
+    ws = torch.empty(fs.workspace_bytes(prob, 3), device="cuda", dtype=torch.uint8)
+    fs.linearno_slice_fwd(prob, up("x"), up("fx"), up("Ws"), up("b"), up("tau"), z, clse, ws)
+    torch.cuda.synchronize()
+    a = (np.einsum("bnhd,dg->bhng", inp["x"].astype(np.float64), inp["Ws"].astype(np.float64)) +
+         inp["b"]) / inp["tau"].astype(np.float64)[None, :, None, None]
+    top = a.max(2)
+    ref = top + np.log(np.exp(a - top[:, :, None]).sum(2))
+    c = Checker(f"merge/{w.name}", "f32")
+    c.add("clse", clse.double().cpu().numpy() * LN2, ref, keep=False)
+    c.add("z", z.double().cpu().numpy(),
+          np.einsum("bhng,bnhv->bhgv", np.exp(a - ref[:, :, None]), inp["fx"].astype(np.float64)),
+          keep=False)
+    c.finish()
