@@ -150,6 +150,10 @@ PassCfg pick_cfg(const Geom& g, Pass pass, int np) {
   // last point are empty (their workgroups exit, their partials are zero).
   if (FS_XCD_CHUNKS && units > 1 && c.chunks >= 8 && c.chunks % 8 != 0)
     c.chunks = (c.chunks + 7) / 8 * 8;
+  // ... and grids that many samples, heads or slot blocks make too long for one wave of workgroups
+  // are grouped in every pass (fp32, 8192 heads, N = 1024, G = 32: forward 1548 us plain, 1397
+  // grouped, backward 1982 and 1759; bf16, 1024 heads, N = 4096, G = 512: 2563 and 2454, 7538 and 7240)
+  c.group = c.group || (int64_t)c.chunks * units > 4096;
   c.nsub = c.chunks;
   c.sub_pts = c.chunk_pts;
   // very long streams of the slice: a chunk's points are sub-chunks of at most FS_MAX_TILES

@@ -101,7 +101,7 @@ struct PassCfg {
   // otherwise): a pass with per-chunk partials keeps its partial count while its workgroups
   // sweep the rows together.
   int64_t nsub, sub_pts;
-  bool group;  // the chunks are capped in length (block_pos)
+  bool group;  // workgroups that share rows are dispatched together (block_pos)
 };
 
 // np > 0: the point group count of PASS_POINT's chunking (the point-owned kernels sweep a
