@@ -67,3 +67,58 @@ def test_linearno_backward_keeps_the_column_normaliser_apart(D, G):
         if not n <= 8e-7:
             bad[k] = n
     assert not bad, bad
+
+
+FLT_MAX = float(np.finfo(np.float32).max)
+
+
+@pytest.mark.parametrize("D,G", SHAPES)
+def test_values_at_the_end_of_the_range(D, G):
+    """Finite values above the largest bf16 (masks of the type's lowest value among them) are split
+    without turning into infinities: a lowest x makes its point's weights one-hot, a lowest fx
+    and dout reach the results like any other value."""
+    from paritycheck import Checker
+    w = small(f"range_D{D}_G{G}", "f32", D, G, O.MIX_IDENTITY, N=500, H=2)
+    announce(f"range {w}")
+    inp = W.make_inputs(w)
+    inp["fx"][0, 41, 0, 5] = -FLT_MAX
+    _, got = run_gpu(w, inp, backward=False)
+    fwd, _ = O.run_inputs(inp, w.mix, w.eps, backward_too=False)
+    c = Checker(f"range/{w.name}", "f32")
+    for k in ("z", "out"):
+        c.add(f"{k}(fx)", got[k], fwd[k], keep=False)
+    inp = W.make_inputs(w)
+    inp["x"][0, 17, 1, 3] = -FLT_MAX
+    _, got = run_gpu(w, inp, backward=False)
+    fwd, _ = O.run_inputs(inp, w.mix, w.eps, backward_too=False)
+    for k in ("z", "s", "out"):
+        c.add(f"{k}(x)", got[k], fwd[k], keep=False)
+    inp = W.make_inputs(w)
+    inp["dout"][0, 7, 0, 3] = -FLT_MAX
+    _, got = run_gpu(w, inp)
+    _, bwd = O.run_inputs(inp, w.mix, w.eps)
+    for k in ("dzmix", "dfx", "dx"):
+        c.add(f"{k}(dout)", got[k], bwd[k], keep=False)
+    c.finish()
+
+
+@pytest.mark.parametrize("D,G", SHAPES)
+def test_infinities_stay_infinities(D, G):
+    """An infinite fx makes its column of the tokens, and of the outputs they reach, infinite with
+    its sign, as a sum of products does, not NaN; every other value stays what it is without it."""
+    w = small(f"inf_D{D}_G{G}", "f32", D, G, O.MIX_IDENTITY, N=500, H=2)
+    announce(f"infinities {w}")
+    inp = W.make_inputs(w)
+    _, clean = run_gpu(w, inp, backward=False)
+    inp["fx"][0, 41, 0, 5] = np.inf
+    inp["fx"][1, 3, 1, 0] = -np.inf
+    _, got = run_gpu(w, inp, backward=False)
+    hit_z, hit_o = np.zeros(got["z"].shape, bool), np.zeros(got["out"].shape, bool)
+    hit_z[0, 0, :, 5] = hit_z[1, 1, :, 0] = True
+    hit_o[0, :, 0, 5] = hit_o[1, :, 1, 0] = True
+    for k, hit in (("z", hit_z), ("out", hit_o)):
+        assert np.array_equal(got[k][~hit], clean[k][~hit]), k
+        assert not np.isfinite(got[k][hit]).any(), k
+    assert np.all(got["z"][0, 0, :, 5] == np.inf) and np.all(got["z"][1, 1, :, 0] == -np.inf)
+    if D * G == 2048:  # (a padding slot's zero weight makes NaN of it)
+        assert np.all(got["out"][0, :, 0, 5] == np.inf) and np.all(got["out"][1, :, 1, 0] == -np.inf)
