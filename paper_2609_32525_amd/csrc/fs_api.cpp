@@ -104,7 +104,7 @@ PassCfg pick_cfg(const Geom& g, Pass pass, int np) {
   // Workgroups along the points per (sample, head[, slot block]): enough to fill 256 CUs
   // several times, but few enough that the per-workgroup partials stay small next to the
   // streamed data.
-  const bool partials = pass != PASS_DESLICE && pass != PASS_STATS && pass != PASS_POINT;
+  const bool partials = pass != PASS_DESLICE && pass != PASS_POINT;
   int target;
   if (c.NS >= 8)
     target = partials ? 256 : 512;

@@ -28,8 +28,7 @@ enum Pass {
   PASS_DESLICE = 1,
   PASS_BWD_A = 2,
   PASS_BWD_B = 3,
-  PASS_STATS = 4,
-  PASS_POINT = 5
+  PASS_POINT = 4
 };
 
 // Slot-blocked family (large G): the slice, backward pass A and the parameter half of
@@ -74,10 +73,6 @@ inline bool deslice_point_owned(const Geom& g) {
 inline int deslice_pt_waves(const Geom& g) { return g.D > 32 ? FS_POINT_WAVES_WIDE : FS_DESLICE_PT_WAVES; }
 #ifndef FS_POINT_WPE
 #define FS_POINT_WPE 3
-#endif
-// The statistics pass of the slot-blocked family: point-owned (1) or cooperative (0).
-#ifndef FS_STATS_POINT
-#define FS_STATS_POINT 1
 #endif
 #ifndef FS_POINT_WPE_MIN
 #define FS_POINT_WPE_MIN 3
@@ -157,7 +152,6 @@ hipError_t run_pass_bwd_a(const Geom& g, const PassArgs& a, hipStream_t st);
 hipError_t run_pass_bwd_b(const Geom& g, const PassArgs& a, hipStream_t st);
 // Slot-blocked family: statistics pass (lse only), slot-owned slice, point-owned backward pass
 // (dx, dfx and per-point (c, tb)), slot-owned parameter half of backward pass B.
-hipError_t run_pass_stats(const Geom& g, const PassArgs& a, hipStream_t st);
 hipError_t run_pass_slice_blk(const Geom& g, const PassArgs& a, hipStream_t st);
 // role: 0 tied; 1 / 2 the untied slice / deslice weights; 3 LinearNO's slice weights (the
 // same roles as run_pass_bwd_b_untied).

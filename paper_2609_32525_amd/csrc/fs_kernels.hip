@@ -50,8 +50,6 @@ PassArgs base_args(const Geom& g, Pass p, int np = 0) {
   return a;
 }
 
-inline hipError_t first_err(hipError_t a, hipError_t b) { return a != hipSuccess ? a : b; }
-
 }  // namespace
 
 // =======================================================================================
@@ -74,7 +72,7 @@ hipError_t launch_slice(const Geom& g, const void* x, const void* fx, const floa
   hipError_t e;
   if (blocked(g)) {
     // statistics pass (lse), then the slot-owned slice reading it
-    PassArgs sa = base_args(g, FS_STATS_POINT ? PASS_POINT : PASS_STATS);
+    PassArgs sa = base_args(g, PASS_POINT);
     sa.x = x;
     sa.Ws = Ws;
     sa.bias = bias;
@@ -83,8 +81,7 @@ hipError_t launch_slice(const Geom& g, const void* x, const void* fx, const floa
     a.lse_in = sa.lse_out;
     e = timed(PASS_SLICE, st, [&] {
       hipError_t e1 = g.D > 32 ? run_pass_stats_stream(g, sa, ws + L.simg, st)
-                               : FS_STATS_POINT ? run_pass_stats_pt(g, sa, st)
-                                                : run_pass_stats(g, sa, st);
+                               : run_pass_stats_pt(g, sa, st);
       return e1 != hipSuccess ? e1 : run_pass_slice_blk(g, a, st);
     });
   } else {

@@ -13,18 +13,12 @@
 namespace fs {
 namespace {
 
-constexpr int kThreads = 256;
 constexpr int kRedThreads = 1024;  // column reductions: many row groups in flight per column
 constexpr int kCols = 64;          // columns per workgroup (chunk reductions)
 constexpr int kRowGroups = kRedThreads / kCols;
 constexpr int kColsWide = 16;      // long reductions (over samples, heads and chunks)
 constexpr int kRowGroupsWide = kRedThreads / kColsWide;
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) v = fmaxf(v, __shfl_xor(v, off));
-  return v;
-}
 
 // ---------------------------------------------------------------------------------------
 // Fixed-order column sums. Thread (row group rg, column cg) sums rows rg, rg + 4, ... of its
