@@ -149,8 +149,9 @@ int fs_mix(const fs_problem* prob, const fs_mix_desc* mix, const float* z, float
  * dz = Mix^T(dzmix) and the mix-parameter gradient (summed over samples and heads; per head
  * for a per-head A): dmix_params is dA (G,G)/(H,G,G) for LINEAR_G, dWc (V,V) for LINEAR_C,
  * [dWq; dWk; dWv] (3,V,V) for ATTN; nullable (skipped). ws/ws_bytes: the backward workspace,
- * fs_workspace_bytes(prob, 1, .) bytes (the attention backward keeps q, k, v and dP there,
- * and the per-(sample, head) parameter partials are summed from it in a fixed order).     */
+ * fs_workspace_bytes(prob, 1, .) bytes (token sets beyond one workgroup keep sums of the token
+ * gradients there, the attention also q, k, v, one value per token and partials of the parameter
+ * gradients, which are summed in a fixed order).                                           */
 int fs_mix_bwd(const fs_problem* prob, const fs_mix_desc* mix, const float* z,
                const float* attn_probs, const float* dzmix, float* dz, float* dmix_params,
                void* ws, size_t ws_bytes, void* hip_stream);

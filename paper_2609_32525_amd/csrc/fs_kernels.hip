@@ -12,8 +12,10 @@ namespace {
 
 // Bytes of pass A's partials per (sample, head) up to which k_tok_bwd sums them itself: one
 // workgroup reads them at one compute unit's rate. At 1 MiB (N = 2^20, G = 64, V = 32) it took
-// 33.2 us, the reduction kernel and k_tok_bwd without the sum 5.1 + 13.7 us; at 256 KiB
-// (N = 32768, G = 32) 14.8 us against 4.2 + 12.5 us and a launch more.
+// 33.2 us, the reduction kernel and k_tok_bwd without the sum 5.1 + 13.7 us. Whole backward, summed
+// there and by the reduction kernel: 256 KiB 73.1 and 72.7 us (fp32, N = 32768, G = 32), 195.5 and
+// 195.5 (N = 2^17, G = 64, V = 16); 512 KiB 63.8 and 61.0 (bf16, N = 32768, G = 64), 139.7 and
+// 137.3 (N = 2^17); 1 MiB 902.9 and 890.1. Up to 256 KiB a launch less is worth as much.
 constexpr int64_t kTokPartBytes = 256 << 10;
 
 // Launch the kernels of one logical streaming pass (f), bracketed by the caller's measurement
