@@ -579,7 +579,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 4)))
   for (int t = 0; t < TPW; ++t) {
     const int ut = w + NW * t;
     if (ut < nt) {
-      s[t] *= inv;
+      // e / L, rounded once (e times the rounded reciprocal left P 1.05 to 1.06 times as far from
+      // 64 bits as before, this 0.85 times)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float p = s[t][r] * inv;
+        s[t][r] = __builtin_fmaf(__builtin_fmaf(-p, L, s[t][r]), inv, p);
+      }
       *reinterpret_cast<f4*>(Pb + (int64_t)(g0 + i) * G + 16 * ut + 4 * j) = s[t];
       tile_rows<V>(T, s[t], zb + 16 * ut * V, i, j);
     }
