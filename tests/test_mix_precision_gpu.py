@@ -82,3 +82,32 @@ def test_mix_bwd_alone_stays_a_matrix_product():
     bwd = us(lambda: fs.mix_bwd(prob, md, z, P, dzm, dz, dm, ws))
     print(f"  forward {fwd:.1f} us, backward {bwd:.1f} us", flush=True)
     assert bwd < 8.0 * fwd
+
+
+def test_attention_probabilities_are_rounded_once():
+    """P = e / L over nearly equal scores: the exponential (an ulp at most, 2^-24 rms over half
+    of it), L's rounding, common to a row, and one rounding of the quotient: 2^-24 / sqrt(3)
+    each, 4.7e-8 measured with the row's common part, 5.2e-8 allowed. A reciprocal rounded first
+    adds another (5.8e-8)."""
+    import torch
+    import paper_2609_32525_amd as fs
+    announce("attention probabilities")
+    B, H, G, V = 1, 8, 256, 32
+    err = []
+    for seed in range(6):
+        g = torch.Generator(device="cuda")
+        g.manual_seed(seed)
+        lim = math.sqrt(6.0 / (2 * V))
+        W = [(torch.rand(V, V, device="cuda", generator=g) * 2 - 1) * lim for _ in range(3)]
+        z = torch.randn(B, H, G, V, device="cuda", generator=g) * 0.05
+        prob = fs.Problem.make(B, 64, H, V, V, G, fs.F32, 1e-5, 0)
+        md = fs.MixDesc.make(fs.MIX_ATTN, Wq=W[0], Wk=W[1], Wv=W[2], scale=1.0 / math.sqrt(V))
+        zmix, P = torch.empty_like(z), torch.empty(B, H, G, G, device="cuda")
+        fs.mix(prob, md, z, zmix, P)
+        torch.cuda.synchronize()
+        zd, Wd = z.double().cpu(), [w.double().cpu() for w in W]
+        ref = torch.softmax((zd @ Wd[0]) @ (zd @ Wd[1]).transpose(2, 3) / math.sqrt(V), -1)
+        err.append(float((P.double().cpu() - ref).norm() / ref.norm()))
+    mean = sum(err) / len(err)
+    print(f"  P {mean:.2e}", flush=True)
+    assert mean <= 5.2e-8, err
